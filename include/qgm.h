@@ -138,7 +138,9 @@ typedef struct {
                              one trip to memory, at 8 B per element */
   double cost;            /* sum over eliminations of 2^deg(v) (Section "Variable elimination") */
   int32_t engine;         /* engine the plan runs with (INTERPRETER, GENERATED or WIDE) */
-  int32_t waves;          /* GENERATED: wavefronts per block the item tree is cut across */
+  int32_t waves;          /* GENERATED: wavefronts per block the item tree is cut across
+                             (large batches of a cut that leaves one block per compute unit
+                             run a one-wavefront form of it, with the same results) */
   double compile_s;       /* seconds spent generating and compiling the plan's kernel */
   int32_t launches;       /* kernel launches of the item steps per pass: WIDE with
                              generated kernels, one per level of mutually independent
@@ -381,7 +383,10 @@ void qgm_graph_free(qgm_graph* g);
  * the generated kernel).  Each feasible variant is generated, compiled,
  * timed on the device for a batch of n_bs bitstrings x n_slices slices (all
  * bits 0, angles 0, 3 warm-up and 10 timed runs with HIP events on `stream`),
- * and the fastest one is kept for the plan.  *waves_out gets the chosen
+ * and the fastest one is kept for the plan.  A plan whose cut has a
+ * one-wavefront form (qgm_stats waves) tries that form for 1; if its own cut
+ * or that form is the fastest, it keeps both, this batch and smaller (larger)
+ * ones running the cut (the form).  *waves_out gets the chosen
  * count.  Other engines: no-op, *waves_out = 1.  The workspace must hold
  * qgm_workspace_size(p, n_bs, n_slices) bytes; its contents are overwritten.
  * Errors: QGM_E_ARG, QGM_E_WORKSPACE, QGM_E_HIP. */

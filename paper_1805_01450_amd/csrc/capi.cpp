@@ -1046,12 +1046,22 @@ qgm_status qgm_plan_autotune(qgm_plan* p, int32_t n_bs, uint64_t n_slices, void*
     int waves = 1;
     float ms = 0;
   };
-  // the current kernel is one candidate
+  // The current cut is one candidate, its one-wavefront form another, which
+  // stands for the cut on one wavefront.  The form is hidden while the others
+  // are timed: a launch would choose it by the batch.
   Variant best;
   best.code = p->code;
   best.mod = (hipModule_t)p->dev.module;
   best.fn = (hipFunction_t)p->dev.chain_fn;
   best.waves = p->dev.chain_waves;
+  const hipFunction_t cut = best.fn;
+  void* const whole = p->dev.whole_fn;
+  p->dev.whole_fn = nullptr;
+  auto run = [&](const Variant& v) {
+    p->dev.module = v.mod;
+    p->dev.chain_fn = v.fn;
+    p->dev.chain_waves = v.waves;
+  };
   auto time_current = [&](float& ms) -> qgm_status {
     std::string err;
     for (int r = 0; r < 13; ++r) {
@@ -1064,9 +1074,19 @@ qgm_status qgm_plan_autotune(qgm_plan* p, int32_t n_bs, uint64_t n_slices, void*
       return fail(QGM_E_HIP, "event timing failed");
     return QGM_OK;
   };
-  if ((s = time_current(best.ms))) return s;
+  s = time_current(best.ms);
+  float whole_ms = best.ms;
+  if (!s && whole) {
+    Variant v = best;
+    v.fn = (hipFunction_t)whole;
+    v.waves = 1;
+    run(v);
+    s = time_current(whole_ms);
+    run(best);
+  }
   for (int w : {1, 2, 4, 8}) {
-    if (w == best.waves) continue;  // the current kernel
+    if (s) break;
+    if (w == best.waves || (w == 1 && whole)) continue;  // the current kernel, or its one-wavefront form
     int got = 0;
     std::string src = generate_chain_source(p->prog, p->opts.prec, p->net.n_qubits, &got, w, p->opts.persistent != 0);
     if (got != w) continue;  // no cut on w wavefronts fits for the plan
@@ -1079,25 +1099,32 @@ qgm_status qgm_plan_autotune(qgm_plan* p, int32_t n_bs, uint64_t n_slices, void*
       continue;
     }
     v.waves = w;
-    p->dev.module = v.mod;
-    p->dev.chain_fn = v.fn;
-    p->dev.chain_waves = w;
+    run(v);
     s = time_current(v.ms);
-    if (s || v.ms >= best.ms) {
+    if (s || v.ms >= std::min(best.ms, whole_ms)) {
       (void)hipModuleUnload(v.mod);
     } else {
       if (best.mod) (void)hipModuleUnload(best.mod);
       best = v;
     }
-    p->dev.module = best.mod;
-    p->dev.chain_fn = best.fn;
-    p->dev.chain_waves = best.waves;
-    if (s) break;
+    run(best);
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   p->code = best.code;
-  p->dev.whole_fn = nullptr;  // the tuned kernel serves every batch
+  if (best.fn == cut) {
+    // the form stays beside its cut; this batch runs the faster of the two
+    p->dev.whole_fn = whole;
+    const uint64_t blocks = ((uint64_t)n_bs * n_slices + 63) / 64;
+    if (!s && whole && whole_ms < best.ms) {
+      p->dev.whole_from = blocks;
+      p->dev.cut_upto = std::min(p->dev.cut_upto, blocks - 1);
+      best.waves = 1;
+    } else if (!s && whole) {
+      p->dev.cut_upto = blocks;
+      if (p->dev.whole_from <= blocks) p->dev.whole_from = UINT64_MAX;
+    }
+  }  // (another cut serves every batch)
   *waves_out = best.waves;
   return s;
   GUARD_END

@@ -65,6 +65,10 @@ struct DevProgram {
   void* whole_module = nullptr;
   void* whole_fn = nullptr;
   int chain_per_cu = 1, whole_per_cu = 1;
+  // What the autotuner measured, which goes before the estimate: batches of up
+  // to cut_upto blocks run the cut, those of whole_from blocks and more the
+  // one-wavefront form.
+  uint64_t cut_upto = 0, whole_from = UINT64_MAX;
   ChainEstimate chain_est, whole_est;
   int chain_persistent = 0;  // 1: the generated kernel pulls chunks from a work queue (resident grid)
   // Constant area computed once per plan (plans without RZ angles): the raw

@@ -845,7 +845,8 @@ namespace {
 // (6x6x25, k = 10, 1024 bitstrings in complex64: one block of 114 KiB per
 // compute unit at a time, 1528 us against 512 us).
 bool use_whole(const DevProgram& dp, uint64_t n_blocks) {
-  if (!dp.whole_fn) return false;
+  if (!dp.whole_fn || n_blocks <= dp.cut_upto) return false;
+  if (n_blocks >= dp.whole_from) return true;
   auto rounds = [&](const ChainEstimate& e, int per_cu) {
     const uint64_t at_once = (uint64_t)std::max(1, dp.n_cu) * std::max(1, per_cu);
     const double full = (double)(n_blocks / at_once), rest = (double)(n_blocks % at_once);
