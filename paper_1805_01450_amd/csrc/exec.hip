@@ -596,17 +596,18 @@ int dev_upload(const Program& prog, const std::vector<char>& code, const WidePro
     }
     dp.module = mod;
     dp.chain_fn = fn;
-    if (whole_code && !whole_code->empty()) {
-      HIP_OK(hipModuleLoadData(&mod, whole_code->data()));
+    // (the form is an addition: a plan for which it does not load or match
+    // runs the cut)
+    if (whole_code && !whole_code->empty() && hipModuleLoadData(&mod, whole_code->data()) == hipSuccess) {
       dp.whole_module = mod;
-      HIP_OK(hipModuleGetFunction(&fn, mod, "qgm_chain"));
-      if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&dp.chain_per_cu, (hipFunction_t)dp.chain_fn,
-                                                             kLanes * dp.chain_waves, 0) != hipSuccess ||
-          hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&dp.whole_per_cu, fn, kLanes, 0) != hipSuccess)
-        (void)hipGetLastError();
-      else if (same_results(dp, fn, n_qubits, elem_bytes))
+      if (hipModuleGetFunction(&fn, mod, "qgm_chain") == hipSuccess &&
+          hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&dp.chain_per_cu, (hipFunction_t)dp.chain_fn,
+                                                             kLanes * dp.chain_waves, 0) == hipSuccess &&
+          hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&dp.whole_per_cu, fn, kLanes, 0) == hipSuccess &&
+          same_results(dp, fn, n_qubits, elem_bytes))
         dp.whole_fn = fn;
     }
+    (void)hipGetLastError();
   }
   HIP_OK(hipGetDevice(&dp.device));
   int rc = dev_query(dp.n_cu, dp.max_lds, err);
