@@ -1054,7 +1054,7 @@ qgm_status qgm_plan_autotune(qgm_plan* p, int32_t n_bs, uint64_t n_slices, void*
   best.mod = (hipModule_t)p->dev.module;
   best.fn = (hipFunction_t)p->dev.chain_fn;
   best.waves = p->dev.chain_waves;
-  const hipFunction_t cut = best.fn;
+  bool own_cut = true;
   void* const whole = p->dev.whole_fn;
   p->dev.whole_fn = nullptr;
   auto run = [&](const Variant& v) {
@@ -1106,13 +1106,14 @@ qgm_status qgm_plan_autotune(qgm_plan* p, int32_t n_bs, uint64_t n_slices, void*
     } else {
       if (best.mod) (void)hipModuleUnload(best.mod);
       best = v;
+      own_cut = false;
     }
     run(best);
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   p->code = best.code;
-  if (best.fn == cut) {
+  if (own_cut) {
     // the form stays beside its cut; this batch runs the faster of the two
     p->dev.whole_fn = whole;
     const uint64_t blocks = ((uint64_t)n_bs * n_slices + 63) / 64;
