@@ -8,11 +8,11 @@
 #include <cstdlib>
 #include <cmath>
 #include <cstring>
+#include <future>
 #include <exception>
 #include <mutex>
 #include <new>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "../../include/qgm.h"
@@ -522,19 +522,31 @@ qgm_status qgm_plan_create(const qgm_circuit* c, const int32_t* sliced_vars, int
     // alongside; with room for two the cut keeps up in large batches (6x6x22,
     // k = 10, 101 bitstrings: 40 against 45 us).  Plans with angles compute
     // constants that depend on them per wavefront and have no such form.
-    std::thread also;
-    if (p->dev.chain_waves > 1 && o.waves == 0 && !o.persistent && p->net.n_params == 0 && p->prog.n_open == 0 &&
-        p->dev.chain_est.lds > 81920)
-      also = std::thread([p, &o] {
+    // (Whatever fails in it leaves the cut; the future waits for it on every
+    // way out of this scope.)
+    std::future<void> also;
+    const auto make_whole = [p, &o] {
+      try {
         int one = 1;
         std::string e;
         const std::string w = generate_chain_source(p->prog, o.prec, p->net.n_qubits, &one, 0, false, true,
                                                     &p->dev.whole_est);
         if (!jit_compile(w, "qgm_chain.hip", p->whole_code, e)) p->whole_code.clear();
-      });
+      } catch (...) {
+        p->whole_code.clear();
+      }
+    };
+    if (p->dev.chain_waves > 1 && o.waves == 0 && !o.persistent && p->net.n_params == 0 && p->prog.n_open == 0 &&
+        p->dev.chain_est.lds > 81920) {
+      try {
+        also = std::async(std::launch::async, make_whole);
+      } catch (const std::system_error&) {  // no thread to be had: after the cut
+        also = std::async(std::launch::deferred, make_whole);
+      }
+    }
     std::string jerr;
     bool ok = jit_compile(src, "qgm_chain.hip", p->code, jerr);
-    if (also.joinable()) also.join();
+    if (also.valid()) also.wait();
     if (const char* dir = std::getenv("QGM_DUMP_DIR")) {
       // debugging aid: keep the generated source and code object
       std::string base = std::string(dir) + "/qgm_chain_" + std::to_string((uintptr_t)p);

@@ -24,11 +24,12 @@ static std::atomic<int> n_compiles{0}, n_loads{0};
 static void* of(const char* lib, const char* name) {
   return dlsym(dlopen((std::string(RUNTIME_DIR "/") + lib).c_str(), RTLD_LAZY), name);
 }
-static bool fails(const char* what) { return std::strcmp(std::getenv("FAIL_SECOND"), what) == 0; }
+static bool fails(const char* what) { return std::strcmp(std::getenv("FAIL"), what) == 0; }
 extern "C" int compiles() { return n_compiles; }
 extern "C" int loads() { return n_loads; }
 extern "C" int hiprtcCreateProgram(void** p, const char* src, const char* name, int n, const char** h, const char** i) {
-  if (++n_compiles > 1 && fails("compile")) throw std::bad_alloc();
+  ++n_compiles;
+  if (fails(std::strstr(src, "int never = 0") ? "form" : "cut")) throw std::bad_alloc();
   static auto f = (int (*)(void**, const char*, const char*, int, const char**, const char**))of("libhiprtc.so", "hiprtcCreateProgram");
   return f(p, src, name, n, h, i);
 }
@@ -46,7 +47,11 @@ import paper_1805_01450_amd as q
 from workload import generate_circuit, random_bitstrings
 c = q.Circuit(generate_circuit(6, 25, 0))
 sl, order = c.plan_slices(k_req=10, time_budget_s=1.0, flags=q.QGM_PLAN_DETERMINISTIC)
-p = q.Plan(c, sl, order, prec=q.QGM_C64)
+try:
+    p = q.Plan(c, sl, order, prec=q.QGM_C64)
+except q.QgmError as e:
+    print(json.dumps({"status": e.status}), flush=True)
+    sys.exit(0)
 out = {"waves": p.stats()["waves"], "compiles": shim.compiles()}
 if sys.argv[2] == "run":
     bits = random_bitstrings(36, 400, 21)
@@ -64,9 +69,17 @@ def _child(tmp_path, fail, what):
                     "-ldl"], check=True)
     root = os.path.dirname(os.path.dirname(os.path.abspath(q.__file__)))
     r = subprocess.run([sys.executable, "-c", CHILD, str(lib), what], cwd=root, capture_output=True, text=True,
-                       timeout=110, env=dict(os.environ, FAIL_SECOND=fail))
+                       timeout=110, env=dict(os.environ, FAIL=fail))
     assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
     return json.loads(r.stdout.splitlines()[-1])
+
+
+def test_exceptions_of_the_two_compiles(tmp_path):
+    """The two kernels compile side by side.  One that throws in the form's
+    leaves the cut; one in the cut's waits for the other and comes back as a
+    status; neither ends the process."""
+    assert _child(tmp_path, "form", "create") == {"waves": 4, "compiles": 2}
+    assert _child(tmp_path, "cut", "create")["status"] != 0
 
 
 @pytest.mark.gpu
