@@ -95,8 +95,10 @@ typedef struct {
   int32_t n_open;            /* open outputs: the number of entries of open_qubits (0..10) */
   const char* tile_table_path; /* WIDE matrix-core steps: a tile table written by
                                 qgm_plan_tune_tiles (read at plan creation; the string is
-                                not kept); steps whose shape has an entry use the tuned
-                                tile parameters; NULL = built-in choice.  An unreadable or
+                                not kept); steps on rows of 64 items whose shape has an
+                                entry use the tuned tile parameters (steps that read or
+                                write a large tensor in quad rows, [item / 4][element]
+                                [item % 4], have fixed ones); NULL = built-in choice.  An unreadable or
                                 malformed table is QGM_E_ARG */
   const int32_t* open_qubits;  /* n_open distinct qubits whose output variables stay open: they
                                 are neither fixed to the bitstring nor summed, so one
@@ -513,9 +515,10 @@ qgm_status qgm_contraction_run(qgm_contraction* c, void* d_mem, int64_t n_groups
 void qgm_contraction_free(qgm_contraction* c);
 
 /* Not in the paper (a launch-shape choice of this library).  Tile autotuner
- * for the matrix-core steps of a WIDE complex64 or BF16x3 plan: for each
- * step shape (ni, nj, nk), largest flops first until 99 % of the plan's
- * matrix-core flops are covered, candidate tiles (block layout and k per
+ * for the matrix-core steps of a WIDE complex64 or BF16x3 plan that work on
+ * rows of 64 items (qgm_plan_opts tile_table_path): for each
+ * step shape (ni, nj, nk), largest flops first until 99 % of those steps'
+ * flops are covered, candidate tiles (block layout and k per
  * stage, then ring budget and band) are generated, compiled and timed on the
  * device as single contractions (qgm_contraction_*; a batch of 64 items with
  * enough batch bits to fill the GPU, at most 8 GiB of operands, allocated
@@ -523,7 +526,7 @@ void qgm_contraction_free(qgm_contraction* c);
  * and the fastest is written to the text table at table_path (entries of
  * other shapes already there are kept).  Plans created with
  * opts.tile_table_path = table_path then use the tuned tiles.  *n_tuned gets
- * the number of shapes tuned (0 for plans without matrix-core steps).
+ * the number of shapes tuned (0 for plans without such steps).
  * Errors: QGM_E_ARG (null, unreadable or unwritable table), QGM_E_HIP. */
 qgm_status qgm_plan_tune_tiles(qgm_plan* p, const char* table_path, void* hip_stream, int32_t* n_tuned);
 

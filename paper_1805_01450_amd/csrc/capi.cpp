@@ -1321,11 +1321,12 @@ qgm_status qgm_plan_tune_tiles(qgm_plan* p, const char* table_path, void* stream
     return QGM_OK;  // no matrix-core steps
   hipStream_t stream = (hipStream_t)stream_;
   // the plan's matrix-core shapes by their flops per item, largest first
+  // (steps on quad rows have fixed tiles)
   std::map<TileKey, double> shape_flops;
   std::map<TileKey, int> shape_nb;
   for (int si = 0; si < p->wide.n_steps; ++si) {
     int nb = 0, ni = 0, nj = 0, nk = 0;
-    if (!mfma_step_shape(p->wide, si, p->opts.prec, nb, ni, nj, nk)) continue;
+    if (step_is_quad(p->wide, si) || !mfma_step_shape(p->wide, si, p->opts.prec, nb, ni, nj, nk)) continue;
     const TileKey key{p->opts.prec, ni, nj, nk};
     shape_flops[key] += std::ldexp(8.0, nb + ni + nj + nk);
     shape_nb[key] = std::max(shape_nb[key], nb);
@@ -1345,6 +1346,11 @@ qgm_status qgm_plan_tune_tiles(qgm_plan* p, const char* table_path, void* stream
       std::fclose(f);
       if (!read_tile_table(table_path, table, terr)) return fail(QGM_E_ARG, terr);
     }
+  }
+  std::string werr;
+  if (order.empty()) {
+    if (!write_tile_table(table_path, table, werr)) return fail(QGM_E_ARG, werr);
+    return QGM_OK;
   }
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
@@ -1481,7 +1487,6 @@ qgm_status qgm_plan_tune_tiles(qgm_plan* p, const char* table_path, void* stream
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (st) return st;
-  std::string werr;
   if (!write_tile_table(table_path, table, werr)) return fail(QGM_E_ARG, werr);
   return QGM_OK;
   GUARD_END

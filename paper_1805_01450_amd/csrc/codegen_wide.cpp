@@ -35,7 +35,7 @@ std::string lit(double v) {
 
 // Whether a step reads or writes a tensor in quad rows; such a step addresses
 // its item tensors through Rows (generate_wide_source).
-static bool step_is_quad(const WideProgram& wide, int si) {
+bool step_is_quad(const WideProgram& wide, int si) {
   const int32_t* sr = &wide.steps[8 * si];
   if (!wide.step_quad.empty() && wide.step_quad[si]) return true;
   for (int i = 0; i < sr[4]; ++i)
@@ -749,24 +749,27 @@ bool emit_mfma_step(std::ostringstream& o, const std::string& pre, WideKernel& k
   const int32_t* Sc = rec.size() == 3 ? rec[2] : nullptr;  // constant scale of the results
   // Tile parameters: a tuned table entry for this shape, else the built-in
   // choice (2 x 2 tiles of 16 items when both sides have 5 bits, two k per
-  // unit, a ring of at most 52 KiB, bands of four j blocks).
+  // unit, a ring of at most 52 KiB, bands of four j blocks).  The table is of
+  // steps on rows of 64 items: on quad rows its entries were slower than the
+  // fixed tiles below (complex64 47 against 43.5 ms), and the form of the
+  // products does not hang on it.
   MfmaTile tp;
-  const bool from_table = table_tile(tiles, prec, (int)bi.size(), (int)bj.size(), ns, tp);
+  const bool from_table = !quad && table_tile(tiles, prec, (int)bi.size(), (int)bj.size(), ns, tp);
   // the per-item form, as many items per block as the level kernel has
   // wavefronts, or the 16-item forms, which need four wavefronts
   {
     MfmaTile t16;
     int it_pref = 4;
     const bool per_item = per_item_choice(prec, from_table, tp, ns, t16, it_pref);
-    // On quad rows complex64 takes it for every sum of two bits and more unless
-    // the table names another form, and every step of it the full tile, two K
+    // On quad rows complex64 takes it for every sum of two bits and more, and
+    // every step of it the full tile, two K
     // steps per stage and a ring of two stages (two blocks per CU): the fastest
     // of eight tiles and rings on each of the nine largest steps of the 8x8x40
     // k = 8 plan, 43.5 ms per 128 slices against 47.2 ms (32 columns) and 48.8
     // ms (32 rows) in complex64, 39.2 ms against 41.8 and 43.0 ms in BF16x3,
     // where one K step per stage took 44.6 ms.
     if (quad) t16 = prec == 0 ? MfmaTile{1, 81920, 0, 0} : MfmaTile{2, 65536, 0, 0};
-    if ((per_item || (quad && (prec == 0 || (prec == 1 && !from_table)))) &&
+    if ((per_item || (quad && prec != 2)) &&
         emit_mfma16_step(&o, pre, k, si, out, r, ns, W, prec, A, B, Sc, bb, bi, bj, t16, true, lds_bytes, quad, out_quad))
       return true;
   }

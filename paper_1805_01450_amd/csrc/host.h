@@ -330,8 +330,8 @@ inline uint64_t group_vary_mask(uint64_t first_group, int n_groups, uint64_t s_b
   }
   return v;
 }
-// Tile parameters of a matrix-core step (two-operand contraction with ni
-// row, nj column and nk summed bits).  per: k steps per LDS stage (one block
+// Tile parameters of a matrix-core step on rows of 64 items (two-operand
+// contraction with ni row, nj column and nk summed bits).  per: k steps per LDS stage (one block
 // barrier each); lds_budget: bytes of LDS the operand ring may take (2..8
 // stages); jband: log2 of the j blocks that run next to each other on one
 // XCD; layout: 0 = built-in (2 x 2 wavefront tiles when both sides have 5
@@ -354,6 +354,9 @@ using TileTable = std::map<TileKey, MfmaTile>;
 // Text form, one entry per line: "prec ni nj nk per lds_budget jband layout";
 // '#' starts a comment.  read: false (with err) on a malformed line.
 bool read_tile_table(const std::string& path, TileTable& t, std::string& err);
+// Whether wide step si reads or writes a tensor in quad rows (the tile table
+// is not for it).
+bool step_is_quad(const WideProgram& wide, int si);
 // (nb, ni, nj, nk) of wide step si when it runs on the matrix cores in
 // precision prec (1 = complex64, 2 = BF16x3).
 bool mfma_step_shape(const WideProgram& wide, int si, int prec, int& nb, int& ni, int& nj, int& nk);

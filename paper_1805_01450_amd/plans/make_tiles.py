@@ -3,7 +3,9 @@
 
     python paper_1805_01450_amd/plans/make_tiles.py [--out PATH] [--no-confirm] [name ...]
 
-Needs a GPU.  The table holds one line per (precision, row bits, column
+Needs a GPU.  Only steps on rows of 64 items take their tiles from the table
+and are tuned: in the 8x8x40 plans without gradients every matrix-core step
+works on quad rows, whose tiles are fixed.  The table holds one line per (precision, row bits, column
 bits, summed bits) shape; shapes already in an existing table at PATH are
 kept unless tuned again.  The tuner times each shape alone, which does not
 see the operand strides and cache state of the plan's own levels; so each
