@@ -479,7 +479,8 @@ def main():
             return None
         return abs(complex(amps[0]) - a128) / max(abs(a128), 2.0 ** (-n * n / 2))
 
-    dtype = {"c64": "c64 (fp32 complex arithmetic, fp64 slice sum)",
+    dtype = {"c64": "c64 (fp32 values and accumulation; products fp32 or, in sums of 32 and more terms over large "
+                    "tensors, six products of exact bf16 parts; fp64 slice sum)",
              "bf16x3": "bf16x3 (three bf16 products per real product, fp32 accumulation, fp64 slice sum)",
              "c128": "c128 (fp64 complex arithmetic)"}[head]
     line = {

@@ -53,7 +53,12 @@ typedef enum {
 
 typedef enum {
   QGM_C128 = 0,  /* complex128 contraction */
-  QGM_C64 = 1,   /* complex64 contraction, FP32 accumulation */
+  QGM_C64 = 1,   /* complex64 contraction, FP32 accumulation.  WIDE: sums of 32 and more terms
+                    over large tensors form a real product from the exact bf16 parts of its
+                    factors, x = xh + xm + xl: xh*yh + xh*ym + xm*yh + xh*yl + xl*yh + xm*ym
+                    (what is left out is below 2^-23 of the product; the sums are as close to
+                    64-bit arithmetic as with FP32 products).  Parts of values below 2^-110
+                    leave the normal range of bf16 */
   QGM_BF16X3 = 2 /* complex64 storage; every real product from bf16 splits x = xh + xl (round to
                     nearest even): xh*yh + xh*yl + xl*yh, accumulated in FP32 */
 } qgm_precision;
