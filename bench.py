@@ -8,7 +8,8 @@ contraction chain (level kernels, matrix cores for the large two-operand
 contractions) and the FP64 compensated slice sum.  Inputs are resident in
 device memory before timing starts.
 
-The headline is complex64 (FP32 arithmetic, FP64 slice sum); BF16x3 and
+The headline is complex64 (FP32 values and accumulation, FP64 slice sum; the
+products of long sums over large tensors from exact bfloat16 parts); BF16x3 and
 complex128 legs of the same workload ride along with their own rates, their
 matrix-core fraction of peak, and the error of each against the FP64 oracle's
 values of single slices (stored by tests/golden/make_stored_plan_slices.py)
@@ -23,7 +24,9 @@ import argparse
 import json
 import math
 import os
+import re
 import sys
+import tempfile
 import time
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
@@ -219,7 +222,47 @@ def timed(q, torch, plan, d_bits, d_part, n_s, steps, warmup, stream):
                 n_runs=n_runs, levels=levels)
 
 
-def level_roofline(levels, workload, prec_name):
+def c64_peaks(source):
+    """Matrix-core peak in useful (complex) flops of each complex64 level
+    kernel, from the generated source: FP32 products run at the FP32 peak,
+    products from exact bfloat16 parts (six per real product) at a sixth of the
+    bfloat16 peak, and a kernel with both in the sum of its steps' times."""
+    peaks = []
+    for kernel in re.split(r'(?=extern "C" __global__ void)', source)[1:]:
+        if not re.search(r"\bwl\d+\(", kernel.split("{", 1)[0]):
+            continue
+        flops = time_s = 0.0
+        for step in kernel.split("  // step ")[1:]:
+            m = re.match(r"\d+ \(matrix cores.*?\) b (\d+) i (\d+) j (\d+) k (\d+)", step)
+            if m:
+                f = 8.0 * 2.0 ** sum(map(int, m.groups()))
+                flops += f
+                time_s += f / (PEAK_BF16_MATRIX_TFLOPS / 6 if "split3(" in step else PEAK_FP32_MATRIX_TFLOPS)
+        peaks.append(flops / time_s if flops else None)
+    return peaks
+
+
+def made_with_peaks(make):
+    """(the plan that make() returns, c64_peaks of its generated kernels)"""
+    with tempfile.TemporaryDirectory() as tmp:
+        before = os.environ.get("QGM_DUMP_DIR")
+        os.environ["QGM_DUMP_DIR"] = tmp
+        try:
+            plan = make()
+        finally:
+            if before is None:
+                del os.environ["QGM_DUMP_DIR"]
+            else:
+                os.environ["QGM_DUMP_DIR"] = before
+        peaks = []
+        for name in os.listdir(tmp):
+            if name.startswith("qgm_wide_"):
+                with open(os.path.join(tmp, name)) as f:
+                    peaks = c64_peaks(f.read())
+    return plan, peaks
+
+
+def level_roofline(levels, workload, prec_name, peaks=()):
     """Roofline of the dominant level kernel (longest HIP-event duration) and
     of the eight longest: the ceiling each is closest to (matrix cores,
     vector ALUs or HBM) and that fraction."""
@@ -230,13 +273,18 @@ def level_roofline(levels, workload, prec_name):
     k_flops = fl_l[i] * items_l
     k_tf = k_flops / (ms_l[i] * 1e-3) / 1e12
     k_gbs = by_l[i] * items_l / (ms_l[i] * 1e-3) / 1e9
-    # matrix-core peak in useful (complex) flops: FP64, or the bfloat16 peak
-    # over the bfloat16 products per real product: three in BF16x3, six in the
-    # large complex64 steps (exact parts of FP32 values; above the FP32 peak)
-    mpeak = {"c128": PEAK_FP64_MATRIX_TFLOPS, "bf16x3": PEAK_BF16_MATRIX_TFLOPS / 3}.get(prec_name,
-                                                                                       PEAK_BF16_MATRIX_TFLOPS / 6)
+    # matrix-core peak in useful (complex) flops: FP64, the bfloat16 peak over
+    # the three products of BF16x3, or in complex64 the kernel's own (c64_peaks)
     vpeak = PEAK_FP64_VECTOR_TFLOPS if prec_name == "c128" else PEAK_FP32_VECTOR_TFLOPS
-    peak = mpeak if mf_l[i] else vpeak
+
+    def peak_of(j):
+        if not mf_l[j]:
+            return vpeak
+        if prec_name != "c64":
+            return PEAK_FP64_MATRIX_TFLOPS if prec_name == "c128" else PEAK_BF16_MATRIX_TFLOPS / 3
+        return (peaks[j] if j < len(peaks) else None) or PEAK_FP32_MATRIX_TFLOPS
+
+    peak = peak_of(i)
     traffic = measured_traffic(workload, f"wl{i}", 1, prec_name)
     # the ceiling the kernel is closest to: its arithmetic (matrix cores or
     # vector ALUs) or HBM
@@ -253,7 +301,7 @@ def level_roofline(levels, workload, prec_name):
     for j in sorted(range(len(ms_l)), key=lambda x: -ms_l[x])[:8]:
         tf = fl_l[j] * items_l / (ms_l[j] * 1e-3) / 1e12
         gb = by_l[j] * items_l / (ms_l[j] * 1e-3) / 1e9
-        pk = mpeak if mf_l[j] else vpeak
+        pk = peak_of(j)
         fr_f, fr_b = tf / pk, gb / PEAK_HBM_GBS
         per_level.append({"kernel": f"wl{j}", "ms": ms_l[j], "tflops": tf, "hbm_gbs": gb,
                           "bound": ("mfma" if mf_l[j] else "alu") if fr_f >= fr_b else "hbm",
@@ -423,14 +471,15 @@ def main():
     ref_slices = golden_slices(plan_name) if (plan_name and n_bs == 1) else {}
     results = {}
     for name in legs:
-        plan = q.Plan(circ, sliced, order, prec=precs[name], profile=True, engine=eng,
-                      vector_only=args.vector_only, workspace_cap=int(args.workspace_gib * (1 << 30)),
-                      tile_table_path=tile_path)
+        plan, peaks = made_with_peaks(lambda: q.Plan(
+            circ, sliced, order, prec=precs[name], profile=True, engine=eng, vector_only=args.vector_only,
+            workspace_cap=int(args.workspace_gib * (1 << 30)), tile_table_path=tile_path))
         st = plan.stats()
         waves = plan.autotune(n_bs, n_s) if st["engine"] == q.QGM_ENGINE_GENERATED else 1
         r = timed(q, torch, plan, d_bits, d_part, n_s, steps, warmup, stream)
         r["stats"] = plan.stats()
         r["waves"] = waves
+        r["peaks"] = peaks
         r["slice_err"] = slice_errors(plan, bits[0], ref_slices) if ref_slices else None
         plan.release_workspace()  # the next precision's plan may need the memory
         del plan
@@ -447,7 +496,7 @@ def main():
     value = n_items / (r["wall"] / steps)
     flops_launch = st["flops_item"] * n_items
     if wide and r["levels"] and r["levels"][0]:
-        roofline = level_roofline(r["levels"], args.workload, head)
+        roofline = level_roofline(r["levels"], args.workload, head, r["peaks"])
     else:
         # The chain kernel is the run's only long kernel.  HIP events around a
         # direct launch add a few microseconds of their own, so the kernel
@@ -530,7 +579,7 @@ def main():
                "slice_rel_error_vs_oracle": rr["slice_err"],
                "amplitude_rel_error_vs_c128": rel_vs_c128(rr["amps"]) if name != "c128" else 0.0}
         if rr["levels"] and rr["levels"][0]:
-            lr = level_roofline(rr["levels"], args.workload, name)
+            lr = level_roofline(rr["levels"], args.workload, name, rr["peaks"])
             leg["dominant_kernel"] = {x: lr[x] for x in ("kernel", "kernel_ms", "achieved", "frac", "bound")}
             if "matrix_core_kernels_tflops" in lr:
                 tf = lr["matrix_core_kernels_tflops"]
