@@ -53,9 +53,10 @@ struct qgm_plan {
   TileTable tiles;                                   // WIDE: matrix-core tile table (opts.tile_table_path)
   std::string tile_table_path;
   // Host memory the device reads and writes in place, for the small inputs
-  // and results of the host-pointer calls (one call at a time holds it)
+  // and results of the host-pointer calls (one call at a time holds it):
+  // allocated with the tables, so that no call allocates; null: calls copy
   std::mutex stage_mu;
-  char* stage = nullptr;
+  char *stage = nullptr, *dev_stage = nullptr;
   ~qgm_plan() {
     if (stage) (void)hipHostFree(stage);
     for (auto& r : runs)
@@ -118,15 +119,9 @@ class HostStage {
  public:
   // inputs then outputs, each at a multiple of 256
   HostStage(qgm_plan* p, size_t in_bytes, size_t out_bytes) : p_(p), out_(align256(in_bytes)) {
-    if (out_bytes > kStageOut || out_ + out_bytes > kStageBytes || !p->stage_mu.try_lock()) return;
+    if (out_bytes > kStageOut || out_ + out_bytes > kStageBytes || !p->dev_stage || !p->stage_mu.try_lock()) return;
     held_ = true;
-    if (!p->stage &&
-        hipHostMalloc((void**)&p->stage, kStageBytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-      (void)hipGetLastError();
-      p->stage = nullptr;
-    }
-    void* d = nullptr;
-    if (p->stage && hipHostGetDevicePointer(&d, p->stage, 0) == hipSuccess) dev_ = (char*)d;
+    dev_ = p->dev_stage;
   }
   ~HostStage() {
     if (held_) p_->stage_mu.unlock();
@@ -154,10 +149,19 @@ bool inputs_in_place(const qgm_plan* p, uint64_t n_items) {
 
 qgm_status ensure_device(qgm_plan* p) {
   std::string err;
+  const bool first = !p->dev.steps;
   int rc = dev_upload(p->prog, p->code, p->engine == QGM_ENGINE_WIDE ? &p->wide : nullptr, p->dev, err,
                       &p->wide_code, &p->wide_kernels, p->levels.tasks.empty() ? nullptr : &p->levels,
                       &p->whole_code, p->net.n_qubits, p->opts.prec == QGM_C128 ? 16 : 8);
   if (rc) return fail((qgm_status)rc, err);
+  if (first) {
+    void* d = nullptr;
+    if (hipHostMalloc((void**)&p->stage, kStageBytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
+      p->stage = nullptr;
+    else if (hipHostGetDevicePointer(&d, p->stage, 0) == hipSuccess)
+      p->dev_stage = (char*)d;
+    (void)hipGetLastError();
+  }
   // constants of plans without angles: contracted once, here, not per run
   // (the generated kernels fold them at compile time)
   if (p->net.n_params == 0 && p->engine != QGM_ENGINE_GENERATED && !p->dev.cst_cached &&
