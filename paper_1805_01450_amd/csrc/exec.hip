@@ -719,12 +719,10 @@ auto level_kernel_of(int items) {
                       : level_kernel<R, 16, LDS>;
 }
 
-// Dynamic LDS beyond 64 KiB for the level kernel of a precision.
-void allow_lds(int prec, int items, int bytes) {
-  const void* f = prec == 0   ? (const void*)level_kernel_of<double, true>(items)
-                  : prec == 2 ? (const void*)level_kernel_of<bfx3, true>(items)
-                              : (const void*)level_kernel_of<float, true>(items);
-  (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+// Dynamic LDS beyond 64 KiB for an interpreter kernel.  Plans share the
+// kernels: the limit is always what a block may have, less the kernel's own.
+void allow_lds(const void* kernel, size_t max_lds) {
+  (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds - 64);
 }
 }  // namespace
 
@@ -751,17 +749,11 @@ int dev_layout(const Program& prog, const DevProgram& dp, const LaunchCfg& cfg, 
                                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, chain_kernel<float, true>, 64, lds);
     if (e != hipSuccess || occ <= 0) occ = (int)std::max<size_t>(1, dp.max_lds / std::max<size_t>(lds, 1));
     per_cu = std::min(occ, 8);
-    if (lds > 65536) {
-      if (cfg.prec == 0)
-        (void)hipFuncSetAttribute((const void*)chain_kernel<double, true>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      else if (cfg.prec == 2)
-        (void)hipFuncSetAttribute((const void*)chain_kernel<bfx3, true>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      else
-        (void)hipFuncSetAttribute((const void*)chain_kernel<float, true>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    }
+    if (lds > 65536)
+      allow_lds(cfg.prec == 0   ? (const void*)chain_kernel<double, true>
+                : cfg.prec == 2 ? (const void*)chain_kernel<bfx3, true>
+                                : (const void*)chain_kernel<float, true>,
+                dp.max_lds);
   }
   // The level kernel takes batches of up to 128 items per compute unit, eight
   // (or fewer, below) and beyond 16 per unit sixteen to a block; larger ones
@@ -796,7 +788,11 @@ int dev_layout(const Program& prog, const DevProgram& dp, const LaunchCfg& cfg, 
       ws.level_items = I;
       ws.use_lds = dp.level_lds;
       ws.lds_bytes = ws.use_lds ? bytes(I) : 0;
-      if (ws.lds_bytes > 65536) allow_lds(cfg.prec, I, (int)ws.lds_bytes);
+      if (ws.lds_bytes > 65536)
+        allow_lds(cfg.prec == 0   ? (const void*)level_kernel_of<double, true>(I)
+                  : cfg.prec == 2 ? (const void*)level_kernel_of<bfx3, true>(I)
+                                  : (const void*)level_kernel_of<float, true>(I),
+                  dp.max_lds);
     }
   }
   if (ws.level_items)

@@ -91,3 +91,17 @@ a = p.amplitudes(random_bitstrings(16, 4, 1))
 print(json.dumps({"in_call": shim.host_allocations() - before, "at_upload": before, "finite": bool(np.isfinite(a).all())}))
 """)
     assert out["finite"] and out["at_upload"] >= 1 and out["in_call"] == 0
+
+
+def test_lds_limits_are_never_lowered(tmp_path):
+    """Plans share the interpreter's kernels, so one plan's limit of dynamic
+    LDS must not replace a higher one that another thread is about to use."""
+    out = _child(tmp_path, r"""
+# level kernels of more and of less LDS, and one wavefront per 64 items
+big, small = (plan(n, d, k, engine=q.QGM_ENGINE_INTERPRETER) for n, d, k in ((6, 20, 6), (5, 20, 6)))
+for p in (big, small, big):
+    for n_bs in (1, 100, 1000):
+        p.workspace(n_bs)
+print(json.dumps({"set": shim.limits_set(), "lowered": shim.limits_lowered()}))
+""")
+    assert out["set"] > 0 and out["lowered"] == 0
