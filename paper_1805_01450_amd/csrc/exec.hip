@@ -506,13 +506,15 @@ int dev_query(int& n_cu, size_t& max_lds, std::string& err) {
 }
 
 // Whether the one-wavefront form `fn` of a generated kernel gives the cut's
-// item results to the bit, on a few bitstrings and slices: both are written
-// for the same roundings, but which product of a sum is contracted is up to
-// the compiler.
+// item results to the bit, on a few bitstrings and slices that have every
+// slice bit at both values: both are written for the same roundings, but which
+// product of a sum is contracted is up to the compiler.
 static bool same_results(const DevProgram& dp, hipFunction_t fn, int n_qubits, int elem_bytes) {
   constexpr int kBs = 6;
-  const unsigned long long n_s = 32;  // (slices beyond the plan's: bits that nothing reads)
-  const size_t bytes = (size_t)kBs * n_s * elem_bytes;
+  // 32 slices from each of four (slices beyond the plan's: bits that nothing reads)
+  const unsigned long long n_s = 32, from[] = {0, ~0ull << 5, 0xAAAAAAAAAAAAAAA0ull, 0x5555555555555540ull};
+  constexpr int kRuns = 4;
+  const size_t run_bytes = (size_t)kBs * n_s * elem_bytes, bytes = kRuns * run_bytes;
   std::vector<uint8_t> bits((size_t)kBs * n_qubits);
   uint32_t x = 12345u;
   for (uint8_t& b : bits) b = (uint8_t)(((x = x * 1664525u + 1013904223u) >> 20) & 1u);
@@ -523,15 +525,16 @@ static bool same_results(const DevProgram& dp, hipFunction_t fn, int n_qubits, i
             hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess;
   void* a_bits = mem + 2 * bytes;
   ok = ok && hipMemcpyAsync(a_bits, bits.data(), bits.size(), hipMemcpyHostToDevice, st) == hipSuccess;
-  for (int v = 0; v < 2 && ok; ++v) {
-    unsigned long long a_ns = n_s, a_sb = 0, a_ni = kBs * n_s, a_nbs = kBs;
+  for (int i = 0; i < 2 * kRuns && ok; ++i) {
+    const int v = i / kRuns, run = i % kRuns;
+    unsigned long long a_ns = n_s, a_sb = from[run], a_ni = kBs * n_s, a_nbs = kBs;
     int a_nq = n_qubits, a_fused = 0, a_log2 = 5;
-    void *null = nullptr, *a_res = mem + v * bytes;
+    void *null = nullptr, *a_res = mem + v * bytes + run * run_bytes;
     const void* a_raw = dp.raw;
     void* args[] = {&a_bits, &a_ns, &a_sb, &a_ni, &a_nbs, &a_nq, &a_fused, &a_log2, &null, &a_res, &null, &null, &a_raw, &null};
     ok = hipModuleLaunchKernel(v ? fn : (hipFunction_t)dp.chain_fn, (unsigned)((kBs * n_s + kLanes - 1) / kLanes), 1, 1,
                                kLanes * (v ? 1 : dp.chain_waves), 1, 1, 0, st, args, nullptr) == hipSuccess &&
-         hipMemcpyAsync(got[v].data(), a_res, bytes, hipMemcpyDeviceToHost, st) == hipSuccess;
+         hipMemcpyAsync(got[v].data() + run * run_bytes, a_res, run_bytes, hipMemcpyDeviceToHost, st) == hipSuccess;
   }
   ok = ok && hipStreamSynchronize(st) == hipSuccess;
   if (st) (void)hipStreamDestroy(st);

@@ -105,3 +105,15 @@ for p in (big, small, big):
 print(json.dumps({"set": shim.limits_set(), "lowered": shim.limits_lowered()}))
 """)
     assert out["set"] > 0 and out["lowered"] == 0
+
+
+def test_one_wavefront_form_is_compared_over_all_slice_bits(tmp_path):
+    """The form is used where it gives the cut's bits; the slices it is
+    compared on (the only launches here) have every slice bit at 0 and at 1."""
+    out = _child(tmp_path, r"""
+p = plan(6, 25, 10, prec=q.QGM_C64)
+p.workspace(1)
+every = (1 << p.k) - 1
+print(json.dumps({"k": p.k, "ones": shim.slice_ones() & every, "zeros": shim.slice_zeros() & every}))
+""")
+    assert out["ones"] == out["zeros"] == (1 << out["k"]) - 1
