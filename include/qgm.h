@@ -224,8 +224,9 @@ qgm_status qgm_plan_slices(const qgm_circuit* c, int32_t k_req, int32_t target_r
  *     WIDE engine compiles it (constant factors combined, small eliminations
  *     absorbed, operand pairs pre-contracted): seconds per slice with the
  *     flops of matrix-core-shaped contractions at 65 TFLOP/s, the other
- *     flops at 30 TFLOP/s and the bytes at 5 TB/s, the rates its kernels
- *     reach on MI355X;
+ *     flops at 30 TFLOP/s and the bytes at 5 TB/s: fixed weights, so that a
+ *     search gives the plans it gave (the long matrix-core sums of large
+ *     tensors now run at 120 to 178 TFLOP/s in complex64);
  *   QGM_PLAN_CHOOSE_K: with SEARCH | WIDE_TIME and k_req >= 0, k_req is the
  *     largest k tried: each k from k_req down to k_req - 6 gets an equal
  *     share of the budget, and the plan with the least predicted time for

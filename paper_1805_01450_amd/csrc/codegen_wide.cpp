@@ -715,7 +715,12 @@ static bool per_item_choice(int prec, bool from_table, const MfmaTile& tp, int n
 // 7x7x30 gradient in complex64 2.16 -> 1.27 ms on the device, the last
 // contraction of the 7x7x30 amplitude in complex128 (1024 outputs, 256 terms)
 // 63 -> 34 us; limits of 2048 and 8192 wavefronts, and sums of 8 or 16 terms,
-// are slower or the same within 1 %.  BF16x3 sums keep their order: at three
+// are slower or the same within 1 %.  The rule counts one group, and many
+// groups fill the chip without a split: 7x7x30 gradients of 1, 2, 4, 8, 16 and
+// 32 bitstrings take 1.49, 2.63, 5.27, 10.1, 19.6 and 39.0 ms in complex128
+// against 2.02, 3.06, 5.52, 10.2, 19.4 and 37.8 without it, in complex64 1.03
+// to 21.3 against 1.55 to 21.5, and amplitudes are the same or faster to 128.
+// BF16x3 sums keep their order: at three
 // products of rounded halves a single amplitude moves by 1e-5 with it.
 constexpr int kSplitRank = 11, kSplitSum = 5;
 constexpr unsigned long long kSplitWaves = 4096;

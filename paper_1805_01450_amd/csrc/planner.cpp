@@ -532,14 +532,16 @@ static bool plan_once(const Network& net, int k_req, int target_rank, double tim
   if (score) {
     if (flags & 16) {
       // the compiled program of the wide engine (with its regroupings):
-      // estimated seconds per slice at the rates those kernels reach
+      // estimated seconds per slice
       Program prog;
       std::string err;
       int code = 0;
       if (!compile_program(net, sliced_vars, order_vars, prog, err, code, false, true)) return false;
-      // seconds per slice at the rates the wide engine reaches on one
-      // MI355X: matrix-core contractions ~65 TFLOP/s, other steps ~30
-      // TFLOP/s, streaming ~5 TB/s; with group sharing, in passes of G
+      // seconds per slice at fixed rates: matrix-core contractions 65 TFLOP/s,
+      // other steps 30 TFLOP/s, streaming 5 TB/s (what the wide engine
+      // reached on one MI355X before quad rows, on which long complex64 sums
+      // run at 120 to 178; other weights would choose other plans); with
+      // group sharing, in passes of G
       // groups (what 96 GiB holds in complex64, at most 4 and 2^(k - 6)),
       // a step independent of the sliced variables at the varying group
       // bits counts 1 / G
