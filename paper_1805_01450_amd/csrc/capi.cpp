@@ -473,6 +473,9 @@ qgm_status qgm_plan_create(const qgm_circuit* c, const int32_t* sliced_vars, int
     // array less 2 MiB for everything else of a group's run
     const double budget = o.workspace_cap ? (double)o.workspace_cap : std::ldexp(1.0, 30) * 96;
     double most = (budget / el - p->prog.n_const) / 64;
+    // a pass keeps its groups, where one of a few would be lost to the growth
+    const double group = p->prog.item_elems * 64.0 * el, groups = std::floor(budget / group);
+    if (groups >= 1 && groups <= 16) most = std::min(most, std::max((double)p->prog.item_elems, budget / groups / 64 / el));
     if ((p->prog.item_elems * 64.0 + p->prog.n_const) * el <= QGM_NOALLOC_SCRATCH_BYTES)
       most = std::min(most, std::max((double)p->prog.item_elems,
                                      ((QGM_NOALLOC_SCRATCH_BYTES - (2 << 20)) / (double)el - p->prog.n_const) / 64));
